@@ -105,13 +105,11 @@ struct LayerW {
 // the key score (x = LayerNorm rows, K = D, W = W_K, pos = null).
 struct EmbedArgs {
   const float* patches;  // [B][N][P] (P = K, the row length of x)
-  const void* w_pe;      // [P][D] storage dtype
+  const void* w_pe;      // packed [D/16][ceil(P/32)][64][8] storage dtype (FixedPackArgs)
   const float* b_pe;     // [D]
   const float* pos;      // [N][D], or null: nothing added after the chain
   float* t0;             // [B][N][D]
   int B, N, P, D, dtype;
-  int* zero;             // counters to clear (may be null)
-  int nzero;
   int* ident_idx;        // if set: idx[v][i] = i, count[v] = N
   int* ident_count;
 };
@@ -253,6 +251,17 @@ struct PackArgs {
   int K, Ncols, kchunks, nblocks, dtype;
 };
 
+// Weights of a fixed-order product (patch embedding, key projection): W [K][D],
+// rows `pitch` elements apart -> [D/16][ceil(K/32)][64 lanes][8]: element s of
+// lane 16 g + n of chunk (b, c) is W[32 c + 4 s + g][16 b + n], zero past K.
+struct FixedPackArgs {
+  const void* src;
+  void* dst;
+  int K, D;
+  long pitch;
+  int dtype;
+};
+
 // Folding a LayerNorm (gamma, beta) into the packed weights W that follow it:
 // W' = S(gamma_k W[k][n]) in the packed layout, c1[n] = sum_k W'[k][n] and
 // c2b[n] = sum_k beta_k W[k][n] + b[n] (fp32, columns up to nblocks * 16).
@@ -328,6 +337,7 @@ hipError_t launch_res(const ResArgs& a, int mmax, hipStream_t s);
 hipError_t launch_hsum(const HsumArgs& a, hipStream_t s);
 hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
+hipError_t launch_fixed_pack(const FixedPackArgs& a, hipStream_t s);
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s);
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 hipError_t launch_export(const ExportArgs& a, hipStream_t s);

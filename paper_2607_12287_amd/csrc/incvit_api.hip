@@ -32,7 +32,7 @@ struct PackedLayer {
 
 struct PackedLayout {
   size_t w_pe, b_pe, pos, lnf_g, lnf_b, total;
-  size_t w_key;  // W_K of layer 0, [D][D] storage dtype (key score)
+  size_t w_key;  // W_K of layer 0, packed like w_pe (key score)
   std::vector<PackedLayer> layers;
 };
 
@@ -113,7 +113,7 @@ PackedLayout packed_layout(const Shape& sh) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
   const int D = sh.D, eb = sh.eb;
-  p.w_pe = take((size_t)sh.P * D * eb);
+  p.w_pe = take((size_t)round_up(sh.P, 32) * D * eb);
   p.b_pe = take((size_t)D * 4);
   p.pos = take((size_t)sh.N * D * 4);
   for (int l = 0; l < sh.L; ++l) {
@@ -651,7 +651,7 @@ incvit_status score_pass(incvit_handle* h, int B, char* ws, const WsLayout& wl, 
   incvit_status st = run(h, INCVIT_K_KEY_LN, s, [&] { return launch_keyln(ka, s); });
   if (st != INCVIT_OK) return st;
   EmbedArgs pa{kn, h->packed + h->pl.w_key, fptr(h, L0.b_qkv) + sh.D, nullptr, key,
-               B, sh.N, sh.D, sh.D, sh.dtype, nullptr, 0, nullptr, nullptr};
+               B, sh.N, sh.D, sh.D, sh.dtype, nullptr, nullptr};
   st = run(h, INCVIT_K_KEY_PROJ, s, [&] { return launch_keyproj(pa, s); });
   if (st != INCVIT_OK) return st;
   *out = key;
@@ -677,7 +677,7 @@ incvit_status full_impl(incvit_handle* h, int32_t B, const float* patches, void*
   float* t0 = reinterpret_cast<float*>(ws + wl.t0);
 
   EmbedArgs ea{patches, h->packed + h->pl.w_pe, fptr(h, h->pl.b_pe), fptr(h, h->pl.pos), t0,
-               B, sh.N, sh.P, sh.D, sh.dtype, nullptr, 0, idx, count};
+               B, sh.N, sh.P, sh.D, sh.dtype, idx, count};
   if ((st = run(h, INCVIT_K_EMBED, s, [&] { return launch_embed(ea, s); })) != INCVIT_OK) return st;
   const float* score = nullptr;
   if ((st = score_pass(h, B, ws, wl, &score, s)) != INCVIT_OK) return st;
@@ -755,7 +755,7 @@ incvit_status incvit_pack_weights(const incvit_config* cfg, const void* canonica
     e = launch_fold(a, s);
   };
   const int D = sh.D;
-  e = hipMemcpyAsync(dst + pl.w_pe, src + cn.w_pe * eb, (size_t)sh.P * D * eb, hipMemcpyDeviceToDevice, s);
+  e = launch_fixed_pack(FixedPackArgs{src + cn.w_pe * eb, dst + pl.w_pe, sh.P, D, D, sh.dtype}, s);
   conv(cn.b_pe, pl.b_pe, D, D);
   conv(cn.pos, pl.pos, (long)sh.N * D, (long)sh.N * D);
   for (int l = 0; l < sh.L; ++l) {
@@ -778,10 +778,9 @@ incvit_status incvit_pack_weights(const incvit_config* cfg, const void* canonica
   }
   conv(cn.lnf_g, pl.lnf_g, D, D);
   conv(cn.lnf_b, pl.lnf_b, D, D);
-  // W_K of layer 0 as its own [D][D] matrix (columns D..2D-1 of W_qkv) for the key score
+  // W_K of layer 0 (columns D..2D-1 of W_qkv) for the key score
   if (e == hipSuccess)
-    e = hipMemcpy2DAsync(dst + pl.w_key, (size_t)D * eb, src + (cn.layers[0].w_qkv + D) * eb, (size_t)3 * D * eb,
-                         (size_t)D * eb, D, hipMemcpyDeviceToDevice, s);
+    e = launch_fixed_pack(FixedPackArgs{src + (cn.layers[0].w_qkv + D) * eb, dst + pl.w_key, D, D, 3 * (long)D, sh.dtype}, s);
   if (e != hipSuccess) return fail(nullptr, INCVIT_ERR_HIP, std::string("pack: ") + hipGetErrorString(e));
   return INCVIT_OK;
 }
@@ -863,7 +862,7 @@ incvit_status incvit_step(incvit_handle* h, int32_t B, const float* patches, voi
     max_rows = std::max(max_rows, c);
   }
   EmbedArgs ea{patches, h->packed + h->pl.w_pe, fptr(h, h->pl.b_pe), fptr(h, h->pl.pos), t0,
-               B, sh.N, sh.P, sh.D, sh.dtype, nullptr, 0, nullptr, nullptr};
+               B, sh.N, sh.P, sh.D, sh.dtype, nullptr, nullptr};
   if ((st = run(h, INCVIT_K_EMBED, s, [&] { return launch_embed(ea, s); })) != INCVIT_OK) return st;
   const float* score = nullptr;
   if ((st = score_pass(h, B, ws, wl, &score, s)) != INCVIT_OK) return st;

@@ -13,22 +13,53 @@
 //   cos: lane j of a wave sums the terms d = j, j+64, ... with fma, the 64
 //        lane partials are combined by the halving tree (offsets 32..1), then
 //        dot / max(sqrt(|a|^2) * sqrt(|b|^2), 1e-8).
-// This is fp32 vector-ALU work (P*D fma per token, D*D more for the key).
+// The products are fp32 matrix-core work (P*D fma per token, D*D more for the key).
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace incvit {
 
-// 16 consecutive bytes of weights and their values as floats
-__device__ __forceinline__ void load16(V8<uint16_t>& v, const uint16_t* p) { v.load(p); }
-__device__ __forceinline__ void load16(V8<float>& v, const float* p) {
-  v.a = __builtin_bit_cast(float4, *(const INCVIT_GLOBAL f32x4_t*)p);
+// The fixed-order product on the matrix cores.  gfx950's fp32 MFMA rounds every
+// multiply-add as one fma and takes k in ascending order, so a chain of
+// v_mfma_f32_16x16x4_f32 over k is bit for bit the scalar fma chain above
+// (checked against host fma chains, denormal results included); it runs at
+// twice the vector units' non-packed fp32 rate and needs no LDS.
+//
+// A wave owns TM x TN tiles of 16 tokens x 16 columns; the product is formed
+// transposed (the weights are the MFMA's A operand), so that a lane ends up
+// with 4 consecutive columns of one token: 16-byte stores.  One MFMA step takes
+// k = 4 s + g from lane group g = lane / 16.
+//   * weights: packed so that one 16-byte load per lane (bf16; two for fp32)
+//     is a 32-deep chunk of 16 columns, k = 32 c + 4 s + g in element s;
+//   * patches: 16-byte loads of 4 consecutive k per lane (64 contiguous bytes
+//     per token and half chunk), then a 4 x 4 transposition between the lane
+//     groups with v_permlane32_swap / v_permlane16_swap, which puts k = 4 s + g
+//     into register s.
+// The loads of PF = 4 chunks are in flight (6 to 9 are slower: more lines than
+// the first-level cache holds).  The four waves of a workgroup take consecutive
+// token tiles of the same columns, so their weight loads meet in that cache.
+// Bound by the waves' chains of dependent MFMAs where tiles are few (147 steps
+// of 32 clocks at P = 588), by the fp32 matrix rate where they are many.
+// Measured, us per launch, against the vector-unit form (LDS-staged, 3 x 2 or
+// 4 x 2 outputs per lane) it replaced: 256 x 588 x 1152 21.0 -> 11.8, 3 streams
+// of that 30.1 -> 18.6, 1024 x 588 x 1152 40.8 -> 25.6, 2048 x 588 x 1024
+// 52.9 -> 31.8, 8192 x 588 x 1024 178 -> 96 (103 TFLOP/s), key projection of
+// 546 x 768 x 768 28.7 -> 15.3.
+
+// register j of lane group g <-> register g of lane group j
+__device__ __forceinline__ void transpose_groups(uint32_t (&r)[4]) {
+  auto s02 = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);
+  auto s13 = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);
+  auto s01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+  auto s23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+  r[0] = s01[0];
+  r[1] = s01[1];
+  r[2] = s23[0];
+  r[3] = s23[1];
 }
-// the same 16 bytes through a buffer resource (lane offset voff, uniform soff)
-__device__ __forceinline__ void bload16(V8<uint16_t>& v, Rsrc r, uint32_t voff, uint32_t soff) { v.bload(r, voff, soff); }
-__device__ __forceinline__ void bload16(V8<float>& v, Rsrc r, uint32_t voff, uint32_t soff) {
-  v.a = bload16f(r, voff, soff);
-}
-__device__ __forceinline__ void unpack16(float* f, const V8<uint16_t>& v) {
+
+__device__ __forceinline__ void chunk_weights(float* f, const V8<uint16_t>& v) {
   const uint32_t q[4] = {v.v.x, v.v.y, v.v.z, v.v.w};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -36,244 +67,144 @@ __device__ __forceinline__ void unpack16(float* f, const V8<uint16_t>& v) {
     f[2 * e + 1] = __uint_as_float(q[e] & 0xffff0000u);
   }
 }
-__device__ __forceinline__ void unpack16(float* f, const V8<float>& v) {
+__device__ __forceinline__ void chunk_weights(float* f, const V8<float>& v) {
   f[0] = v.a.x; f[1] = v.a.y; f[2] = v.a.z; f[3] = v.a.w;
+  f[4] = v.b.x; f[5] = v.b.y; f[6] = v.b.z; f[7] = v.b.w;
 }
 
-// Workgroup: 4*TM tokens x 64*TN columns; wave w computes tokens
-// TM*w..TM*w+TM-1 of the tile and lane l one column (TN = 1: column l) or two
-// adjacent ones (TN = 2, bf16 weights: columns 2l, 2l+1, kept in LDS as one
-// packed pair), so a k step reads TM + 1 values from LDS for TM*TN fma.  k is
-// staged through LDS in tiles of 64, double buffered, with one barrier per
-// tile.  A tile's global loads go out two tiles of compute ahead into one of
-// three register slots (the loop body is unrolled over the slots, so no
-// register copy waits on a load in flight); every load is unconditional
-// (clamped addresses; values past P are loaded but never used because the k
-// loop stops at P).  The patch tiles sit first in LDS and every buffer stays
-// below 64 KB, so each LDS read is a base register plus an immediate offset.
-template <class T, int NT, int TM, int TN>
+template <class T, int TM, int TN>
 __device__ __forceinline__ void embed_body(const EmbedArgs& a) {
-  static_assert(TN == 1 || (TN == 2 && sizeof(T) == 2), "two columns per lane need bf16 weights");
-  constexpr int TT = 4 * TM, TC = 64 * TN;  // tile tokens, tile columns
-  constexpr int WV = 16 / sizeof(T);  // weights per 16-byte load
-  constexpr int WL = 64 * TC / (256 * WV);  // weight loads per thread per tile
-  constexpr int XL = 64 * TT / 256;  // patch loads per thread per tile (= TM)
-  constexpr int XB = 64 * TT;  // floats per patch buffer
-  constexpr int WB = 64 * 64;  // 32-bit words per weight buffer (one per lane and k)
-  __shared__ __align__(16) float smem[2 * XB + 2 * WB];
-  float* const sx = smem;                                            // [buffer][k][token]
-  float* const swf = smem + 2 * XB;                                  // TN = 1: [buffer][k][column]
-  uint32_t* const swp = reinterpret_cast<uint32_t*>(smem + 2 * XB);  // TN = 2: [buffer][k][lane] pairs
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int PF = 4;            // chunks in flight
+  constexpr int TT = 4 * TM * 16;  // tokens per workgroup
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, n = lane & 15;
   // Workgroups are dealt to the 8 XCDs round robin by linear launch index, and
   // each XCD has its own L2.  Renumber them XCD-major (a bijection) and take
   // (stream, column block, token group) from the new number, so that the
   // workgroups of one column block sit on one XCD (at most two): its weights
   // come from HBM once rather than once per XCD.
-  const int ntg = gridDim.x, ncb = gridDim.y;
-  const int total = ntg * ncb * gridDim.z;
-  const int i = blockIdx.x + ntg * (blockIdx.y + ncb * blockIdx.z);
+  const int N = a.N, P = a.P, D = a.D;
+  const int ntg = (N + TT - 1) / TT, ncb = D / (16 * TN);
+  const int total = ntg * ncb * a.B;
+  const int i = blockIdx.x;
   const int x = i % 8, q = total / 8, rem = total % 8;
   const int pos = x * q + min(x, rem) + i / 8;
   const int v = pos / (ncb * ntg), cb = (pos / ntg) % ncb, tg = pos % ntg;
-  const int tok0 = tg * TT, c0 = cb * TC;
-  const int N = a.N, P = a.P, D = a.D;
 
-  if (tg == 0 && cb == 0) {
-    for (int k = tid; k < a.nzero && v == 0; k += 256) a.zero[k] = 0;
-    if (a.ident_idx) {
-      for (int k = tid; k < N; k += 256) a.ident_idx[v * N + k] = k;
-      if (tid == 0) a.ident_count[v] = N;
-    }
+  if (tg == 0 && cb == 0 && a.ident_idx) {
+    for (int k = tid; k < N; k += 256) a.ident_idx[v * N + k] = k;
+    if (tid == 0) a.ident_count[v] = N;
   }
+  const int tok0 = tg * TT + w * TM * 16;  // first token of this wave
+  if (tok0 >= N) return;                   // uniform; no barriers below
 
-  // Operands through buffer loads: every lane offset below is fixed for the
-  // whole kernel and the tile's k position is a wave-uniform offset, so a
-  // fetch needs no address registers.  Reads past the buffer return zero; reads
-  // past a row's end (k >= P) are never used because the k loop stops at P.
+  const int nc = (P + 31) / 32;
   const Rsrc rx = make_rsrc(a.patches + (size_t)v * N * P, (uint32_t)((size_t)N * P * 4));
-  const Rsrc rw = make_rsrc(a.w_pe, (uint32_t)((size_t)P * D * sizeof(T)));
-  uint32_t xoff[XL], woff[WL];
-  // patch element e of a tile: token e / 64, k e % 64 (a wave reads 64
-  // consecutive k of one token's row)
+  const size_t wblk = (size_t)nc * kChunkElems;  // elements of one 16-column block
+  const T* wbase = static_cast<const T*>(a.w_pe) + (size_t)cb * TN * wblk;
+  const Rsrc rw = make_rsrc(wbase, (uint32_t)(TN * wblk * sizeof(T)));
+  uint32_t xoff[TM];
 #pragma unroll
-  for (int j = 0; j < XL; ++j) {
-    const int e = tid + 256 * j;
-    xoff[j] = (uint32_t)((min(tok0 + (e >> 6), N - 1) * P + (e & 63)) * 4);
-  }
-  // weight run e of a tile: row k = e / (TC / WV), WV columns from (e % (TC / WV)) * WV
-#pragma unroll
-  for (int j = 0; j < WL; ++j) {
-    const int e = tid + 256 * j;
-    woff[j] = (uint32_t)(((e / (TC / WV)) * D + min(c0 + (e % (TC / WV)) * WV, D - WV)) * sizeof(T));
-  }
-  struct Tile {
-    float x[XL];
-    V8<T> wv[WL];
-  };
-  auto fetch = [&](Tile& t, int kt) {
-#pragma unroll
-    for (int j = 0; j < XL; ++j)
-      t.x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, xoff[j], (uint32_t)kt * 4, 0));
-#pragma unroll
-    for (int j = 0; j < WL; ++j) bload16(t.wv[j], rw, woff[j], (uint32_t)(kt * D * sizeof(T)));
-  };
-  auto stage = [&](const Tile& t, int b) {
-#pragma unroll
-    for (int j = 0; j < XL; ++j) {
-      const int e = tid + 256 * j;
-      sx[b * XB + (e & 63) * TT + (e >> 6)] = t.x[j];
-    }
-#pragma unroll
-    for (int j = 0; j < WL; ++j) {
-      const int e = tid + 256 * j;
-      const int k = e / (TC / WV), c = (e % (TC / WV)) * WV;
-      if constexpr (TN == 2) {
-        // 8 bf16 columns = 4 packed pairs, stored as they came
-        *reinterpret_cast<uint4*>(&swp[b * WB + k * 64 + c / 2]) = __builtin_bit_cast(uint4, t.wv[j]);
-      } else {
-        float f[WV];
-        unpack16(f, t.wv[j]);
-#pragma unroll
-        for (int q = 0; q < WV; ++q) swf[b * WB + k * 64 + c + q] = f[q];
-      }
-    }
-  };
+  for (int t = 0; t < TM; ++t) xoff[t] = (uint32_t)((min(tok0 + 16 * t + n, N - 1) * P + 4 * g) * 4);
+  const uint32_t woff = (uint32_t)(lane * 8 * sizeof(T));
 
-  // the lane's columns: TN = 1: c0 + lane; TN = 2: c0 + 2 lane and the next
-  const int dl = c0 + (TN == 2 ? 2 * lane : lane);
-  float acc[TM][TN], posv[TM][TN];
+  struct Chunk {
+    float4 x[TM][2];
+    V8<T> w[TN];
+  };
+  auto fetch = [&](Chunk& ch, int c) {
 #pragma unroll
-  for (int n = 0; n < TN; ++n) {
-    const int d = min(dl + n, D - 1);
-    const float bias = a.b_pe[d];
+    for (int b = 0; b < TN; ++b) ch.w[b].bload(rw, woff, (uint32_t)((b * wblk + (size_t)c * kChunkElems) * sizeof(T)));
 #pragma unroll
-    for (int r = 0; r < TM; ++r) {
-      acc[r][n] = bias;
-      const int tok = min(tok0 + TM * w + r, N - 1);
-      posv[r][n] = a.pos ? a.pos[(size_t)tok * D + d] : 0.0f;
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) ch.x[t][h] = bload16f(rx, xoff[t], (uint32_t)(32 * c + 16 * h) * 4);
+  };
+  f32x4_t acc[TM][TN];
+  float4 posv[TM][TN];
+#pragma unroll
+  for (int b = 0; b < TN; ++b) {
+    const int d = (cb * TN + b) * 16 + 4 * g;
+    const float4 bias = *reinterpret_cast<const float4*>(a.b_pe + d);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      acc[t][b] = f32x4_t{bias.x, bias.y, bias.z, bias.w};
+      const int tok = min(tok0 + 16 * t + n, N - 1);
+      posv[t][b] = a.pos ? *reinterpret_cast<const float4*>(a.pos + (size_t)tok * D + d) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
   }
-  // one k step: TM patch values (the same for the whole wave) and TN weights
-  // (TN = 2: one packed bf16 pair), read from LDS, then the TM * TN fma
-  struct Ops {
-    float x[TM];
-    uint32_t w;
-  };
-  auto read_ops = [&](Ops& o, int b, int kk) {
-    if constexpr (TN == 2) o.w = swp[b * WB + kk * 64 + lane];
-    else o.w = __float_as_uint(swf[b * WB + kk * 64 + lane]);
-    if constexpr (TM == 4) {
-      const float4 x4 = *reinterpret_cast<const float4*>(&sx[b * XB + kk * TT + 4 * w]);
-      o.x[0] = x4.x; o.x[1] = x4.y; o.x[2] = x4.z; o.x[3] = x4.w;
-    } else {
+  // the 8 steps of a chunk (steps: how many of them hold k < P; values past P
+  // within a step are zeroed on both sides)
+  auto compute = [&](const Chunk& ch, auto last, int c) {
+    constexpr bool LAST = decltype(last)::value;
+    float wv[TN][8];
 #pragma unroll
-      for (int r = 0; r < TM; ++r) o.x[r] = sx[b * XB + kk * TT + TM * w + r];
-    }
-  };
-  auto fma_ops = [&](const Ops& o) {
-    float wv[TN];
-    if constexpr (TN == 2) {
-      wv[0] = __uint_as_float(o.w << 16);
-      wv[1] = __uint_as_float(o.w & 0xffff0000u);
-    } else {
-      wv[0] = __uint_as_float(o.w);
-    }
+    for (int b = 0; b < TN; ++b) chunk_weights(wv[b], ch.w[b]);
 #pragma unroll
-    for (int r = 0; r < TM; ++r)
+    for (int h = 0; h < 2; ++h) {
+      const int k0 = 32 * c + 16 * h;
+      uint32_t xr[TM][4];
 #pragma unroll
-      for (int n = 0; n < TN; ++n) acc[r][n] = __fmaf_rn(o.x[r], wv[n], acc[r][n]);
-  };
-  auto kstep = [&](int b, int kk) {
-    Ops o;
-    read_ops(o, b, kk);
-    fma_ops(o);
-  };
-  // A full tile of 64 k steps with each step's LDS reads issued PD steps
-  // ahead of its fma: with one wave per SIMD nothing else hides the LDS
-  // latency (the fma order is unchanged).
-  constexpr int PD = 4;
-  auto full_tile = [&](int b) {
-    Ops o[PD];
+      for (int t = 0; t < TM; ++t) {
+        const float xs[4] = {ch.x[t][h].x, ch.x[t][h].y, ch.x[t][h].z, ch.x[t][h].w};
 #pragma unroll
-    for (int p = 0; p < PD; ++p) read_ops(o[p], b, p);
+        for (int j = 0; j < 4; ++j) xr[t][j] = !LAST || k0 + 4 * g + j < P ? __float_as_uint(xs[j]) : 0u;
+        transpose_groups(xr[t]);
+      }
 #pragma unroll
-    for (int kk = 0; kk < 64; ++kk) {
-      const Ops cur = o[kk % PD];
-      if (kk + PD < 64) read_ops(o[kk % PD], b, kk + PD);
-      fma_ops(cur);
-    }
-  };
-  auto compute = [&](int b, int kmax) {
-    if (kmax == 64) {  // uniform
-      full_tile(b);
-      return;
-    }
-#pragma unroll 8
-    for (int kk = 0; kk < kmax; ++kk) kstep(b, kk);
-  };
-  Tile tl[3];
-  fetch(tl[0], 0);
-  fetch(tl[1], 64);
-  fetch(tl[2], 128);
-  stage(tl[0], 0);
-  __syncthreads();
-  if constexpr (NT > 0) {
-    // NT = ceil(P / 64) tiles, unrolled: every slot and buffer index is a
-    // constant, so each wait covers exactly the loads of the tile it stages
+      for (int s = 0; s < 4; ++s) {
+        if (LAST && k0 + 4 * s >= P) continue;  // uniform
 #pragma unroll
-    for (int it = 0; it < NT; ++it) {
-      if (it + 1 < NT) {
-        full_tile(it & 1);
-        stage(tl[(it + 1) % 3], (it + 1) & 1);
-        if (it + 3 < NT) fetch(tl[it % 3], 64 * (it + 3));
-        __syncthreads();
-      } else {
-        compute(it & 1, P - 64 * it);
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+            acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[b][4 * h + s], __uint_as_float(xr[t][s]), acc[t][b], 0, 0, 0);
       }
     }
-  } else {
-    const int nt = (P + 63) / 64;
-    for (int i0 = 0; i0 < nt; i0 += 3) {
+  };
+  // chunk c sits in register slot c % PF; a slot is refilled right after its use
+  Chunk ch[PF];
 #pragma unroll
-      for (int s3 = 0; s3 < 3; ++s3) {
-        const int it = i0 + s3;
-        if (it < nt) {  // uniform
-          // tile it is in LDS buffer it & 1; tile it + 1 waits in slot (s3 + 1) % 3
-          // and is staged after the compute; slot s3 (tile it, already staged)
-          // then takes tile it + 3, whose loads have two tiles of compute to land
-          const int b = it & 1;
-          compute(b, min(64, P - 64 * it));
-          if (it + 1 < nt) stage(tl[(s3 + 1) % 3], b ^ 1);
-          fetch(tl[s3], 64 * (it + 3));
-          __syncthreads();
-        }
-      }
+  for (int p = 0; p < PF; ++p) fetch(ch[p], p);  // past the end: zeros or unused data of the next row
+  const int full = P / 32;  // chunks without a tail
+  int c = 0;
+  for (; c + PF <= full; c += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      compute(ch[p], std::false_type{}, c + p);
+      fetch(ch[p], c + p + PF);
     }
   }
 #pragma unroll
-  for (int n = 0; n < TN; ++n) {
-    const int d = dl + n;
-    if (d < D) {
+  for (int p = 0; p < PF; ++p)
+    if (c + p < nc) compute(ch[p], std::true_type{}, c + p);  // uniform
+
 #pragma unroll
-      for (int r = 0; r < TM; ++r) {
-        const int tok = tok0 + TM * w + r;
-        if (tok < N) a.t0[((size_t)v * N + tok) * D + d] = a.pos ? __fadd_rn(acc[r][n], posv[r][n]) : acc[r][n];
-      }
+  for (int t = 0; t < TM; ++t) {
+    const int tok = tok0 + 16 * t + n;
+    if (tok >= N) continue;
+#pragma unroll
+    for (int b = 0; b < TN; ++b) {
+      float4 o = make_float4(acc[t][b][0], acc[t][b][1], acc[t][b][2], acc[t][b][3]);
+      if (a.pos)
+        o = make_float4(__fadd_rn(o.x, posv[t][b].x), __fadd_rn(o.y, posv[t][b].y), __fadd_rn(o.z, posv[t][b].z),
+                        __fadd_rn(o.w, posv[t][b].w));
+      *reinterpret_cast<float4*>(a.t0 + ((size_t)v * N + tok) * D + (cb * TN + b) * 16 + 4 * g) = o;
     }
   }
 }
 
-template <class T, int NT, int TM, int TN>
+template <class T, int TM, int TN>
 __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
-  embed_body<T, NT, TM, TN>(a);
+  embed_body<T, TM, TN>(a);
 }
 
 // The key projection of the key score: the same fixed-order product with
 // x = LayerNorm rows, K = D, W = W_K of layer 0, no position term.
-template <class T, int NT, int TM, int TN>
+template <class T, int TM, int TN>
 __global__ __launch_bounds__(256) void keyproj_kernel(EmbedArgs a) {
-  embed_body<T, NT, TM, TN>(a);
+  embed_body<T, TM, TN>(a);
 }
 
 // Correctly rounded fp32 square root.  HIP's __fsqrt_rn is the bare hardware
@@ -371,90 +302,30 @@ __global__ __launch_bounds__(256) void sim_kernel(SimArgs a) {
   }
 }
 
-// Tile counts of the shapes in use are compiled unrolled (patch 14 and 16 with
-// 3 channels: P = 588, 768; D = 192, 1024, 1152); other lengths run the loop.
-template <class T, int TM, int TN, template <class, int, int, int> class Launch>
-hipError_t launch_nt(const EmbedArgs& a, dim3 grid, hipStream_t s) {
-  switch ((a.P + 63) / 64) {
-    case 3: return Launch<T, 3, TM, TN>::go(a, grid, s);
-    case 10: return Launch<T, 10, TM, TN>::go(a, grid, s);
-    case 12: return Launch<T, 12, TM, TN>::go(a, grid, s);
-    case 16: return Launch<T, 16, TM, TN>::go(a, grid, s);
-    case 18: return Launch<T, 18, TM, TN>::go(a, grid, s);
-    default: return Launch<T, 0, TM, TN>::go(a, grid, s);
-  }
-}
-template <class T, int NT, int TM, int TN>
-struct EmbedLaunch {
-  static hipError_t go(const EmbedArgs& a, dim3 g, hipStream_t s) {
-    return launch_k(embed_kernel<T, NT, TM, TN>, g, dim3(256), 0, s, a);
-  }
-};
-template <class T, int NT, int TM, int TN>
-struct KeyLaunch {
-  static hipError_t go(const EmbedArgs& a, dim3 g, hipStream_t s) {
-    return launch_k(keyproj_kernel<T, NT, TM, TN>, g, dim3(256), 0, s, a);
-  }
-};
-
-// Register tile of the fixed-order product, TM tokens x TN columns per lane,
-// chosen per shape.  Per k step a CU's LDS returns 4 waves x 64 lanes x
-// (TM + 1) words at 128 bytes per clock, 8 (TM + 1) clocks, while each SIMD
-// spends 4 clocks per wave64 instruction on TM TN fma (and two more to unpack a
-// bf16 pair); the workgroups run in ceil(count / 256) rounds of one per CU.
-// The tile with the fewest estimated clocks wins (the first listed on a tie).
-struct Tiling {
-  int tm, tn;
-};
-constexpr Tiling kTilings[] = {{4, 1}, {3, 2}, {4, 2}};
-
-// fp32 weights take one column per lane only
-inline int pick_tiling(const EmbedArgs& a) {
-  int best = 0;
-  long best_cost = -1;
-  for (int t = 0; t < (a.dtype ? (int)(sizeof(kTilings) / sizeof(kTilings[0])) : 1); ++t) {
-    const int tm = kTilings[t].tm, tn = kTilings[t].tn;
-    const long wgs = (long)((a.N + 4 * tm - 1) / (4 * tm)) * ((a.D + 64 * tn - 1) / (64 * tn)) * a.B;
-    const long step = std::max(8 * (tm + 1), 4 * (tm * tn + (tn == 2 ? 2 : 0)));
-    const long cost = (wgs + 255) / 256 * step;
-    if (best_cost < 0 || cost < best_cost) {
-      best = t;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
-template <class T, template <class, int, int, int> class Launch>
-hipError_t launch_tiled(const EmbedArgs& a, hipStream_t s) {
-  const int t = pick_tiling(a);
-  const int tm = kTilings[t].tm, tn = kTilings[t].tn;
-  const dim3 grid((a.N + 4 * tm - 1) / (4 * tm), (a.D + 64 * tn - 1) / (64 * tn), a.B);
-  // two columns per lane: the patch lengths in use (10 and 12 tiles) run
-  // unrolled, longer rows the tile loop (unrolled over 16 or more tiles the
-  // compiler's hoisting exceeds the register file and spills)
-  if constexpr (sizeof(T) == 2) {
-    const int nt = (a.P + 63) / 64;
-    if (t == 1) {
-      if (nt == 10) return Launch<T, 10, 3, 2>::go(a, grid, s);
-      if (nt == 12) return Launch<T, 12, 3, 2>::go(a, grid, s);
-      return Launch<T, 0, 3, 2>::go(a, grid, s);
-    }
-    if (t == 2) {
-      if (nt == 10) return Launch<T, 10, 4, 2>::go(a, grid, s);
-      if (nt == 12) return Launch<T, 12, 4, 2>::go(a, grid, s);
-      return Launch<T, 0, 4, 2>::go(a, grid, s);
-    }
-  }
-  return launch_nt<T, 4, 1, Launch>(a, grid, s);
+// Tiles per wave, by the number of 16 x 16 output tiles (the chip has 1024
+// SIMDs): one while they are about two per SIMD or fewer, so that every SIMD
+// has a chain to run (1152 tiles 11.8 us against 13.5 with 1 x 2; 2304 tiles
+// 14.8 against 16.7); then 1 x 2, which reads each token row for 32 columns
+// (3456 tiles 18.6 against 20.2); and 2 x 4 from 16 tiles per SIMD on, where
+// operand reads set the pace (32768 tiles 96 against 103; 8192 tiles equal).
+template <class T, bool KEY>
+hipError_t launch_product(const EmbedArgs& a, hipStream_t s) {
+  auto go = [&](auto kernel, int tm, int tn) {
+    const int tt = 64 * tm;
+    return launch_k(kernel, dim3((a.N + tt - 1) / tt * (a.D / (16 * tn)) * a.B), dim3(256), 0, s, a);
+  };
+  const long tiles = (long)a.B * ((a.N + 15) / 16) * (a.D / 16);
+  if (tiles <= 2560) return KEY ? go(keyproj_kernel<T, 1, 1>, 1, 1) : go(embed_kernel<T, 1, 1>, 1, 1);
+  if (tiles < 16384 || a.D % 64) return KEY ? go(keyproj_kernel<T, 1, 2>, 1, 2) : go(embed_kernel<T, 1, 2>, 1, 2);
+  return KEY ? go(keyproj_kernel<T, 2, 4>, 2, 4) : go(embed_kernel<T, 2, 4>, 2, 4);
 }
 
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
-  return a.dtype ? launch_tiled<uint16_t, EmbedLaunch>(a, s) : launch_tiled<float, EmbedLaunch>(a, s);
+  return a.dtype ? launch_product<uint16_t, false>(a, s) : launch_product<float, false>(a, s);
 }
 
 hipError_t launch_keyproj(const EmbedArgs& a, hipStream_t s) {
-  return a.dtype ? launch_tiled<uint16_t, KeyLaunch>(a, s) : launch_tiled<float, KeyLaunch>(a, s);
+  return a.dtype ? launch_product<uint16_t, true>(a, s) : launch_product<float, true>(a, s);
 }
 
 hipError_t launch_keyln(const KeyLnArgs& a, hipStream_t s) {

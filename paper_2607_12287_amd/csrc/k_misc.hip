@@ -22,6 +22,22 @@ __global__ void pack_kernel(PackArgs a) {
   }
 }
 
+// Weights of the fixed-order products in their own operand order (FixedPackArgs).
+template <class T>
+__global__ void fixed_pack_kernel(FixedPackArgs a) {
+  const T* src = static_cast<const T*>(a.src);
+  T* dst = static_cast<T*>(a.dst);
+  const int nc = (a.K + 31) / 32;
+  const size_t total = (size_t)(a.D / 16) * nc * kChunkElems;
+  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
+    const int st = (int)(e & 7), lane = (int)((e >> 3) & 63);
+    const size_t ch = e >> 9;
+    const int c = (int)(ch % nc), b = (int)(ch / nc);
+    const int k = 32 * c + 4 * st + (lane >> 4), col = 16 * b + (lane & 15);
+    dst[e] = k < a.K ? src[(size_t)k * a.pitch + col] : T(0);
+  }
+}
+
 // One thread per packed column: the folded weights of the column (rounded to
 // the storage type), their sum, and beta^T W + b, both accumulated in fp64.
 template <class T>
@@ -111,6 +127,11 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s) {
   if (a.dtype) (void)launch_k(pack_kernel<uint16_t>, dim3(1024), dim3(256), 0, s, a);
   else (void)launch_k(pack_kernel<float>, dim3(1024), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+hipError_t launch_fixed_pack(const FixedPackArgs& a, hipStream_t s) {
+  if (a.dtype) return launch_k(fixed_pack_kernel<uint16_t>, dim3(1024), dim3(256), 0, s, a);
+  return launch_k(fixed_pack_kernel<float>, dim3(1024), dim3(256), 0, s, a);
 }
 
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s) {
