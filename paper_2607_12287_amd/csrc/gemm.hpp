@@ -65,13 +65,14 @@ namespace incvit {
 constexpr int kGemmWaves = 8;
 constexpr int kGemmRB = 32;                       // rows per block: two 16-row MFMA tiles
 
-// GELU, tanh form, with tanh(u) = 1 - 2 / (1 + e^(2u)) on the hardware
-// exponential (error a few fp32 ulps, far below the bf16 rounding that
-// follows; the limits u -> +-inf give +-1).
+// GELU, tanh form: 0.5 x (1 + tanh u) = x / (1 + e^(-2u)), u = sqrt(2/pi)
+// (x + 0.044715 x^3), on the hardware's exponential and reciprocal (one ulp
+// each, and no cancellation for negative x).  e^(-2u) overflows to infinity
+// for x below about -10, whose reciprocal gives the limit -0.
 __device__ __forceinline__ float gelu_tanh(float x) {
-  const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-  const float t = 1.0f - __fdividef(2.0f, 1.0f + __expf(2.0f * u));
-  return 0.5f * x * (1.0f + t);
+  constexpr float c = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
+  const float e = __builtin_amdgcn_exp2f(x * fmaf(x * x, c * 0.044715f, c));
+  return x * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
 template <int EPI>
