@@ -314,15 +314,15 @@ void incvit_graph_destroy(incvit_graph* g);
  * workgroups: one per CU; MLP up projection: two per CU; K-split MLP down
  * projection: one per CU; output projection: all), the rest looping over the
  * row blocks.
- * tiled: the large-row GEMM of bf16 models (output tiles of 64 or 128 rows
- * by 128 columns, K staged through LDS), used where the call's row count is
- * known on the host and at least 512 (full encodes of several streams or of
- * 448x448 frames, pure top-k steps of that many rows, the all-rows MLP):
- * 0 = automatic (used there; the output projection only once its 64-row
- * tiles number 256 or more), 1 = never (the weight-streaming GEMM above).
+ * tiled: the large-row GEMM of bf16 models (output tiles of 64 x 64 to 256 x
+ * 256, K staged through LDS): 0 = automatic, by the call's rows where they are
+ * known on the host (full encodes, pure top-k steps, the all-rows MLP), else by
+ * 32 * row_groups: every GEMM from 512 known rows, the QKV and MLP up
+ * projections from 192, the MLP up projection of more than 4096 columns from 96
+ * (known or not); 1 = never (the weight-streaming GEMM above).
  * The cols and row_groups fields do not apply to its launches; its MLP down
  * projection follows fc2_mode (1: split over K with the row kernel, 2:
- * unsplit; 0: split while its 64-row tiles give fewer than 256 workgroups).
+ * unsplit; 0: split while its 64 x 128 tiles number fewer than 128).
  * A NULL pointer restores the defaults. */
 typedef struct {
   int32_t cols[4];

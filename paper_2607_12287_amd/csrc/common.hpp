@@ -22,9 +22,6 @@ constexpr int kStatusNonFinite = -1;           // a step saw a NaN similarity
 // 16-column block is one 16-byte (bf16) or 32-byte (fp32) load per lane,
 // already in MFMA operand order.
 constexpr int kGemmRows = 64;
-// Calls of bf16 models with at least this many rows known on the host run
-// the large-row GEMM (gemm_tiled.hpp) instead of the weight-streaming one.
-constexpr int kTiledMinRows = 512;
 constexpr int kChunkElems = 512;  // 64 lanes x 8 elements
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
@@ -331,8 +328,8 @@ hipError_t launch_sim(const SimArgs& a, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_commit(const RowsArgs& a, int mmax, hipStream_t s);
 hipError_t launch_gemm(int epi, int cols, const GemmArgs& a, hipStream_t s);
-// the large-row GEMM (gemm_tiled.hpp): bf16, whole K, rows = the call's M
-hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int rows, hipStream_t s);
+// the large-row GEMM (gemm_tiled.hpp): bf16; at most `rows` rows, tiled for `expected`
+hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int expected, int rows, hipStream_t s);
 hipError_t launch_res(const ResArgs& a, int mmax, hipStream_t s);
 hipError_t launch_hsum(const HsumArgs& a, hipStream_t s);
 hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, hipStream_t s);
@@ -410,6 +407,7 @@ __device__ __forceinline__ float4 bload16f(Rsrc r, uint32_t voff, uint32_t soff)
 // 8 consecutive elements of one lane: one MFMA operand for a 32-deep chunk.
 template <class T> struct V8;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 template <> struct V8<uint16_t> {
   uint4 v;
@@ -502,19 +500,8 @@ __host__ __device__ __forceinline__ size_t v_elem(const Shape& sh, int h, int to
 // 15:14; expcnt and lgkmcnt left at their no-wait maxima).
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// 16 bytes of LDS at byte address addr + off (off a compile-time constant)
-// into a register quad, without a wait: the caller waits for lgkmcnt.
-__device__ __forceinline__ void lds_read16(u32x4_t& out, uint32_t addr, int off) {
-  switch (off) {  // the offset is an immediate of the instruction
-#define INCVIT_DSR(o) \
-    case o: asm volatile("ds_read_b128 %0, %1 offset:" #o : "=v"(out) : "v"(addr)); break;
-    INCVIT_DSR(0) INCVIT_DSR(1024) INCVIT_DSR(2048) INCVIT_DSR(3072) INCVIT_DSR(4096) INCVIT_DSR(5120)
-    INCVIT_DSR(6144) INCVIT_DSR(7168) INCVIT_DSR(8192) INCVIT_DSR(9216) INCVIT_DSR(10240) INCVIT_DSR(11264)
-    INCVIT_DSR(12288) INCVIT_DSR(13312) INCVIT_DSR(14336) INCVIT_DSR(15360)
-#undef INCVIT_DSR
-    default: asm volatile("ds_read_b128 %0, %1" : "=v"(out) : "v"(addr + off)); break;
-  }
-}
+// s_waitcnt immediate that waits for every LDS operation and scalar load only.
+__host__ __device__ constexpr int lgkmcnt0_imm() { return 15 | (3 << 14) | (7 << 4); }
 
 // The offsets above separate into a row (token) part and a column (dim) part,
 // so an epilogue that writes many rows of the same columns forms each part

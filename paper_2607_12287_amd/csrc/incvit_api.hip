@@ -445,22 +445,45 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
   const Meta* mmeta = all ? reinterpret_cast<const Meta*>(ws + wl.meta_all) : meta;
   const int mlp_rows = all ? mall : mmax;
   const int mgroups = all ? groups_for(mall, true) : rgroups;
-  // the large-row GEMM: bf16 models, the rows of the call known on the host
-  // and at least kTiledMinRows (full encodes, pure top-k steps, the all-rows
-  // MLP); the output projection only once its tiles fill the chip, and the
-  // MLP down projection split over K while they do not (below)
-  const bool tiled_att = h->tiled == 0 && sh.dtype && exact_m && mmax >= kTiledMinRows;
-  const bool tiled_mlp = h->tiled == 0 && sh.dtype && (exact_m || all) && mlp_rows >= kTiledMinRows;
-  // the large-row MLP down projection runs over K = F: its workgroup's chunks
-  // follow one another, so while its tiles give fewer than one workgroup per
-  // CU it is split over K like the small-M form (partial sums added by the
-  // row kernel): So400m at 768 and 1024 rows, 36-37 us for the whole K in
-  // one workgroup
+  // The large-row GEMM (bf16 models) by the rows that the call has, where they
+  // are known on the host, or else those that the caller expects (row_groups).
+  // us per launch, large-row against small-M form, So400m widths:
+  //   MLP up from 192 known rows: 256 rows 12.0 against 20.0; and from 96 rows
+  //     if it has more than 256 column blocks, which the small-M form takes two
+  //     to a workgroup and one row group: 101 rows 11.3 against 13.3 (with 256
+  //     blocks, ViT-L, 172 rows 10.5 against 9.9);
+  //   QKV from 192 known rows: 256 rows 9.9 against 14.0 (128 rows 10.2
+  //     against 8.6);
+  //   output projection from 512 known rows: 512 rows 8.1 against 9.2, 1024
+  //     rows 9.0 against 13.6 (256 rows 8.1 against 6.3);
+  //   MLP down from 512 known rows;
+  // MLP up and QKV below 512 rows only where 64 x 64 tiles come to at least
+  // half of the CUs.
+  const bool tiled_ok = h->tiled == 0 && sh.dtype;
+  const int exp_rows = exact_m ? mmax : std::min(mmax, 32 * h->row_groups);
+  const bool mlp_known = exact_m || all;
+  const int exp_mlp = all ? mlp_rows : exp_rows;
+  auto tiles64 = [&](int rows, int nout) { return (rows + 63) / 64 * ((nout + 63) / 64); };
+  auto tiled_of = [&](int kind) {
+    if (!tiled_ok) return false;
+    const bool mlp = kind == G_FC1 || kind == G_FC2;
+    const int r = mlp ? exp_mlp : exp_rows;
+    const bool known = mlp ? mlp_known : exact_m;
+    if (known && r >= 512) return true;
+    if (kind == G_FC1) return ((known && r >= 192) || (r >= 96 && sh.Fpad / 16 > 256)) && tiles64(r, sh.Fpad) >= 128;
+    return kind == G_QKV && known && r >= 192 && tiles64(r, 3 * sh.D) >= 128;
+  };
+  const bool tiled_fc2 = tiled_of(G_FC2);
+  // The large-row MLP down projection runs over K = F: its workgroup's chunks
+  // follow one another, so while 64 x 128 tiles leave more than half of the CUs
+  // idle it is split over K like the small-M form (partial sums added by the
+  // row kernel): So400m at 512 rows 11.7 + 5.8 us against 18.9, at 1024 rows
+  // 17.7 + 8.8 against 24.1.
   int fc2_split = 1;
-  if (tiled_mlp) {
+  if (tiled_fc2) {
     const GemmGeom g2 = gemm_geom(sh, G_FC2);
     const int tiles = (mlp_rows + 63) / 64 * ((g2.nblocks + 7) / 8);
-    if (h->fc2_mode == 1 || (h->fc2_mode == 0 && tiles < 256)) fc2_split = g2.ksplit;
+    if (h->fc2_mode == 1 || (h->fc2_mode == 0 && tiles < 128)) fc2_split = g2.ksplit;
   }
   for (int l = 0; l < sh.L; ++l) {
     const PackedLayer& P = h->pl.layers[l];
@@ -473,18 +496,12 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
     // M is known on the host and at least 192; the large-row form whenever it
     // is not split over K (above)
     const bool down = !all && l + 1 < sh.L &&
-                      (tiled_mlp ? fc2_split == 1
+                      (tiled_fc2 ? fc2_split == 1
                                  : h->fc2_mode == 2 || (h->fc2_mode == 0 && exact_m && mmax >= 192));
     auto gemm = [&](int kind, int kernel_kind) -> incvit_status {
       GemmGeom g = gemm_geom(sh, kind);
       const bool mlp = kind == G_FC1 || kind == G_FC2;
-      // the output projection (N = D) takes the large-row form only once its
-      // 64-row tiles fill the chip: with fewer its workgroups each run the
-      // whole K while most CUs idle (So400m at 512 / 768 / 1024 rows: 13.6 /
-      // 14.0 / 13.5 us against 8.3 / 10.9 / 12.7 us for the small-M form; 8
-      // ViT-L streams, 2048 rows and 256 tiles: 13.0 against 14.1 us)
-      const bool tiled = mlp ? tiled_mlp
-                             : tiled_att && (kind != G_OPROJ || (mmax + 63) / 64 * ((g.nblocks + 7) / 8) >= 256);
+      const bool tiled = tiled_of(kind);
       if (kind == G_FC2 && down) g.ksplit = 1;
       else if (kind == G_FC2 && tiled) g.ksplit = fc2_split;
       GemmArgs a;
@@ -534,7 +551,7 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
           break;
       }
       if (tiled)
-        return run(h, kernel_kind, s, [&] { return launch_gemm_tiled(epi, a, mlp ? mlp_rows : mmax, s); });
+        return run(h, kernel_kind, s, [&] { return launch_gemm_tiled(epi, a, mlp ? exp_mlp : exp_rows, mlp ? mlp_rows : mmax, s); });
       const int cols = cols_of(h->cols, g, kind, a.rgroups, mlp ? mlp_rows : mmax, exact_m || (mlp && all));
       return run(h, kernel_kind, s, [&] { return launch_gemm(epi, cols, a, s); });
     };
@@ -548,7 +565,7 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
       r.sh = sh;
       r.layer = l;
       r.part = reinterpret_cast<const float*>(ws + wl.part);
-      r.ksplit = tiled_mlp ? fc2_split : g.ksplit;
+      r.ksplit = tiled_fc2 ? fc2_split : g.ksplit;
       r.mpad = wl.Mpad;
       r.N = sh.N;
       r.res = ws + wl.h;
