@@ -332,7 +332,7 @@ hipError_t launch_gemm(int epi, int cols, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int expected, int rows, hipStream_t s);
 hipError_t launch_res(const ResArgs& a, int mmax, hipStream_t s);
 hipError_t launch_hsum(const HsumArgs& a, hipStream_t s);
-hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, hipStream_t s);
+hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, bool known, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_fixed_pack(const FixedPackArgs& a, hipStream_t s);
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s);

@@ -600,7 +600,7 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
       aa.qmax = wl.Mpad - 1;
       aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)sh.dh));
       const int qtiles = attn_qtiles_of(h->attn_qtiles, B, sh.H, sh.N, max_rows_per_view, exact_m);
-      if ((st = run(h, INCVIT_K_ATTN, s, [&] { return launch_attn(aa, max_rows_per_view, qtiles, h->attn_waves, s); })) != INCVIT_OK)
+      if ((st = run(h, INCVIT_K_ATTN, s, [&] { return launch_attn(aa, max_rows_per_view, qtiles, h->attn_waves, exact_m, s); })) != INCVIT_OK)
         return st;
       if ((st = gemm(G_OPROJ, INCVIT_K_OPROJ)) != INCVIT_OK) return st;
     }

@@ -31,7 +31,22 @@ __device__ __forceinline__ void store4<float>(float* dst, const float* v) {
   *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-constexpr int kMaxDT = kMaxHeadDim / 16;  // 16-wide d tiles
+// max and sum over the four lane groups g (lanes n, n + 16, n + 32, n + 48):
+// gfx950's row and half swaps on the vector unit, no trip through LDS
+__device__ __forceinline__ float group_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float y = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ __forceinline__ float group_sum(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float y = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
 
 // K/V operands of one 32-key block come straight from the cache, which stores
 // them in operand order (k_elem / v_elem): every load is one contiguous
@@ -170,12 +185,12 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
   }
 
   for (int kb = kb0; kb < kb1; kb += GB) {
-    if (kb > kb0) load_group(kb);
 #pragma unroll
     for (int b = 0; b < GB; ++b) {
       if (kb + b < kb1) {  // uniform
         const int key0 = (kb + b) * 32;
-        if (key0 + 32 > N) {  // the stream's last, partial block (uniform)
+        const bool part = key0 + 32 > N;  // the stream's last, partial block (uniform)
+        if (part) {
 #pragma unroll
           for (int t = 0; t < NDTU; ++t) mask_v(vop[b][t], key0 + 8 * g, N);
         }
@@ -191,26 +206,25 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
           // st[t][i] = score of key key0 + 8g + 4t + i for query n of tile qt
           // (the cache's key order within a block), so slot 4t + i of this
           // lane is key 8g + 4t + i: the P operand order of the V product
-          float sc[8];
+          if (part) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (key0 + 8 * g + 4 * t + i >= N) st[t][i] = -INFINITY;
+          }
           float mloc = -INFINITY;
 #pragma unroll
           for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int key = key0 + 8 * g + 4 * t + i;
-              const float x = key < N ? st[t][i] * a.scale_log2 : -INFINITY;
-              sc[4 * t + i] = x;
-              mloc = fmaxf(mloc, x);
-            }
-          mloc = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
-          mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-          const float m_new = fmaxf(m_run[qt], mloc);
-          const bool none = (m_new == -INFINITY);
-          const float alpha = none ? 1.0f : exp2f(m_run[qt] - m_new);
+            for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, st[t][i]);
+          const float m_new = fmaxf(m_run[qt], group_max(mloc) * a.scale_log2);
+          const float m_sub = m_new == -INFINITY ? 0.0f : m_new;  // no key yet: every p is 0
+          const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_sub);
           float p[8], psum = 0.0f;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            p[j] = none ? 0.0f : exp2f(sc[j] - m_new);
+            p[j] = __builtin_amdgcn_exp2f(fmaf(st[j >> 2][j & 3], a.scale_log2, -m_sub));
             psum += p[j];
           }
           l_run[qt] = l_run[qt] * alpha + psum;
@@ -223,14 +237,17 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
           }
           m_run[qt] = m_new;
         }
+        // this block's operands are used up: the block GB further on takes
+        // their registers while the blocks between are worked on
+        if (kb + b + GB < kb1) {  // uniform
+          load_kblock<T, NDC>(kop[b], kbase, kb + b + GB, dh, g, lane);
+          load_vblock<T, NDT, NDTU>(vop[b], vbase, kb + b + GB, lane);
+        }
       }
     }
   }
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    l_run[qt] += __shfl_xor(l_run[qt], 16, 64);
-    l_run[qt] += __shfl_xor(l_run[qt], 32, 64);
-  }
+  for (int qt = 0; qt < QT; ++qt) l_run[qt] = group_sum(l_run[qt]);
 
   // merge: every wave publishes (max, sum, O) of its keys (a wave without keys
   // publishes max = -inf, sum = 0, O = 0); then each wave combines the KW
@@ -260,7 +277,7 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
 #pragma unroll
     for (int ww = 0; ww < KW; ++ww) {
       const float mw = s_m[(ww * QT + qt) * 16 + n];
-      const float f = mw == -INFINITY ? 0.0f : exp2f(mw - mm);
+      const float f = mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - mm);
       lsum += f * s_l[(ww * QT + qt) * 16 + n];
       acc += s_o[((ww * QT + qt) * NDTU + t) * 64 + lane] * f;
     }
@@ -295,7 +312,8 @@ template <class T, int NDC, int NDT, int NDTU, int QT>
 static void launch_t(const AttnArgs& a, int kw, dim3 grid, hipStream_t s) {
   // two key blocks in flight per wave where the registers allow
   constexpr int kGB = NDT <= (sizeof(T) == 2 ? 6 : 4) ? 2 : 1;
-  if (kw == 2) launch_g<T, NDC, NDT, NDTU, kGB, QT, 2>(a, grid, s);
+  if (kw == 1) launch_g<T, NDC, NDT, NDTU, kGB, QT, 1>(a, grid, s);
+  else if (kw == 2) launch_g<T, NDC, NDT, NDTU, kGB, QT, 2>(a, grid, s);
   else if (kw == 4) launch_g<T, NDC, NDT, NDTU, kGB, QT, 4>(a, grid, s);
   else launch_g<T, NDC, NDT, NDTU, kGB, QT, 8>(a, grid, s);
 }
@@ -315,8 +333,9 @@ static void launch_dh(const AttnArgs& a, int kw, dim3 grid, hipStream_t s) {
 // qtiles: 16-query tiles per workgroup (1 or 2).  One tile per workgroup
 // doubles the workgroups (and the K/V reads) for short per-stream row counts;
 // two halve the K/V traffic when there are many rows.  waves: 2, 4 or 8 per
-// workgroup; 0 = about two key blocks per wave.
-hipError_t launch_attn(const AttnArgs& a0, int max_rows_per_view, int qtiles, int waves, hipStream_t s) {
+// workgroup; 0 = by the number of workgroups (known: every workgroup launched
+// has rows).
+hipError_t launch_attn(const AttnArgs& a0, int max_rows_per_view, int qtiles, int waves, bool known, hipStream_t s) {
   AttnArgs a = a0;
   if (!a.sh.dtype) qtiles = 1;
   const int qrows = 16 * qtiles;
@@ -324,7 +343,15 @@ hipError_t launch_attn(const AttnArgs& a0, int max_rows_per_view, int qtiles, in
   if (grid.z == 0) return hipSuccess;
   a.nspec = qtiles == 1 ? 2 : 1;
   const int nkb = a.sh.Npad / 32;
-  const int kw = waves > 0 ? waves : nkb >= 16 ? 8 : 4;
+  // Each wave of a workgroup takes a share of the keys, and the shares are
+  // merged through LDS.  While the workgroups are few, about two key blocks per
+  // wave keep every wave's chain short; once there are enough of them that
+  // fewer waves each still give every SIMD two, a longer run per wave does
+  // without most of the merging.
+  int kw = waves > 0 ? waves : nkb >= 16 ? 8 : 4;
+  const long groups = (long)grid.x * grid.y * grid.z;
+  if (waves == 0 && known)
+    while (kw > 1 && groups * (kw / 2) >= 2048) kw /= 2;
   if (!a.sh.dtype) launch_dh<float, 1>(a, kw, grid, s);  // fp32 operands: one tile (registers)
   else if (qtiles == 1) launch_dh<uint16_t, 1>(a, kw, grid, s);
   else launch_dh<uint16_t, 2>(a, kw, grid, s);
