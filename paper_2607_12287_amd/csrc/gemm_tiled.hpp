@@ -525,8 +525,10 @@ hipError_t launch_tiled_cfg(const GemmArgs& a, int rows, hipStream_t s) {
 //     is full to three quarters, or is the only one: MLP down of 8192 rows 63
 //     (128 x 128: 75), QKV of 8192 rows 71 (74), MLP up of 1024 rows 22.4
 //     (24.4);
-//   128 x 128, two workgroups per CU, for the rest: QKV of 1024 rows 15.8
-//     (64 x 128: 20), MLP up of 512 rows 14.9 (64 x 128: 19.3).
+//   128 x 128 for the rest: QKV of 1024 rows 15.8 (64 x 128: 20), MLP up of
+//     512 rows 14.9 (64 x 128: 19.3); with at most one per CU its ring takes
+//     the whole LDS, more ahead of weights that come from HBM: QKV of 1024
+//     rows within the 448x448 encode 20.1 -> 17.6; else two per CU.
 template <int EPI>
 hipError_t launch_tiled_epi(const GemmArgs& a, int expected, int rows, hipStream_t s) {
   if (!a.sh.dtype || a.ksplit < 1 || a.sh.dh % 8) return hipErrorInvalidValue;
@@ -544,6 +546,7 @@ hipError_t launch_tiled_epi(const GemmArgs& a, int expected, int rows, hipStream
   }
   const int l = tiles(256, 128);
   if (l > 128 && (l <= 256 || full(l, 3))) return launch_tiled_cfg<EPI, 256, 128, 4, 1, 6>(a, rows, s);
+  if (tiles(128, 128) <= 256) return launch_tiled_cfg<EPI, 128, 128, 2, 1, 8>(a, rows, s);
   return launch_tiled_cfg<EPI, 128, 128, 2, 1, 4>(a, rows, s);
 }
 
