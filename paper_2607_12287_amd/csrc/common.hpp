@@ -202,6 +202,7 @@ struct ResArgs {
   int last;           // after the last layer: final LayerNorm
   const float* part;  // [ksplit][mpad][D]
   int ksplit, mpad;
+  int ahead;          // rows below this load before the row count is read
   const void* res;    // H (storage type, operand order)
   const float* bias;
   const float* ln_g;  // the final LayerNorm (last layer)

@@ -567,6 +567,7 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
       r.part = reinterpret_cast<const float*>(ws + wl.part);
       r.ksplit = tiled_fc2 ? fc2_split : g.ksplit;
       r.mpad = wl.Mpad;
+      r.ahead = mlp_known ? mlp_rows : 32;
       r.N = sh.N;
       r.res = ws + wl.h;
       r.bias = fptr(h, P.b_2);

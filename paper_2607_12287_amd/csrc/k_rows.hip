@@ -64,8 +64,10 @@ __global__ __launch_bounds__(256) void res_kernel(ResArgs a) {
   __shared__ float s_red[4];
   const int tid = threadIdx.x, r = blockIdx.x;
   const int M = a.meta->m;
-  // the first 32 rows load before M is known; later rows (rarely used) check first
-  if (r >= 32 && r >= M) return;
+  // the rows that are likely there load before M is known: the first 32, or all
+  // that are launched when the host knows the call's rows; later rows (rarely
+  // used) check first
+  if (r >= a.ahead && r >= M) return;
   const int D = a.sh.D, D4 = D / 4;
   const RowInfo ri = a.rows[r];
 
