@@ -77,6 +77,17 @@ __device__ __forceinline__ void stage_kb(const u32x4_t& rsrc, uint32_t voff, uin
 }
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
 
+// Slots that the staging runs ahead of the products.  One barrier per slot, in
+// its last step: behind the barrier of slot q every wave has multiplied, and so
+// read, slot q - 1 to the end, and may still be reading slot q.  The staging of
+// a slot's first step refills the slot that is free then: q - 1 when that step
+// is behind the barrier (a slot of one step), else q - 2.
+template <int BM, int WR, int KD, int NS>
+__host__ __device__ constexpr int tiled_ahead() {
+  static_assert(NS >= 3, "a slot being read, one landing and one being refilled");
+  return KD == 1 && BM / 16 / WR <= 4 ? NS - 1 : NS - 2;
+}
+
 // workgroups that a CU holds (its LDS is 160 KB; with two, 128 registers a lane)
 template <int EPI, int BM, int BN, int KD, int NS>
 __host__ __device__ constexpr int tiled_per_cu() {
@@ -98,13 +109,8 @@ __global__ __launch_bounds__(512, (2 * tiled_per_cu<EPI, BM, BN, KD, NS>())) voi
   // chunk.  The fragments of a step are read while the step before it is
   // multiplied, into the other of two register sets (W: per chunk).
   constexpr int H = TR > 4 ? TR / 2 : TR, HS = TR / H, S = HS * KD;
-  // One barrier per slot, in its last step: behind the barrier of slot q every
-  // wave has multiplied, and so read, slot q - 1 to the end, and may still be
-  // reading slot q.  The staging of a slot's first step refills the slot that
-  // is free then: q - 1 when that step is behind the barrier (S = 1), else
-  // q - 2; so the stream runs AHEAD slots ahead of the first.
-  constexpr int AHEAD = S == 1 ? NS - 1 : NS - 2;
-  static_assert(NS >= 3, "a slot being read, one landing and one being refilled");
+  constexpr int AHEAD = tiled_ahead<BM, WR, KD, NS>();
+  static_assert(AHEAD == (S == 1 ? NS - 1 : NS - 2), "see tiled_ahead");
   extern __shared__ __align__(16) char smem[];
   float2* s_ps = reinterpret_cast<float2*>(smem + tiled_ring_bytes<BM, BN, KD, NS>());  // [BM] (sum, sum of squares)
 
@@ -152,10 +158,11 @@ __global__ __launch_bounds__(512, (2 * tiled_per_cu<EPI, BM, BN, KD, NS>())) voi
   // first.  A row tile, column block or chunk past its operand's end stages the
   // last one instead, whose products are skipped or never stored.  The stream
   // of slots runs AHEAD ahead of the products and on into the workgroup's next
-  // tile (the launch gives a workgroup several tiles only if each has at least
-  // NS - 1 slots); past the last tile the resources' sizes are zero, so the
-  // loads move nothing and every slot still counts LPW loads: the K loop has
-  // neither branches nor wait counts that depend on the position.
+  // tile (the launch gives a workgroup several tiles only if each has more than
+  // AHEAD slots, so that the tile after the staged one is known when it ends);
+  // past the last tile the resources' sizes are zero, so the loads move nothing
+  // and every slot still counts LPW loads: the K loop has neither branches nor
+  // wait counts that depend on the position.
   auto rsrc_of = [](const void* p, uint32_t bytes) {
     const uint64_t b = reinterpret_cast<uint64_t>(p);
     return u32x4_t{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, bytes, 0x00020000u};
@@ -502,9 +509,10 @@ hipError_t launch_tiled_cfg(const GemmArgs& a, int rows, hipStream_t s) {
   int gm = 1;
   while ((gm + 1) * (gm + 1) * BM <= per_xcd * BN) ++gm;
   b.rgroups = std::max(1, std::min(gm, mt));
-  // several tiles to a workgroup only if each has the slots that the ring runs ahead
+  // several tiles to a workgroup only if each has more slots than the staging
+  // runs ahead
   const int kper = (a.kchunks + a.ksplit - 1) / a.ksplit, klast = a.kchunks - kper * (a.ksplit - 1);
-  const bool shared = (std::min(kper, klast) + KD - 1) / KD >= NS - 1;
+  const bool shared = (std::min(kper, klast) + KD - 1) / KD > tiled_ahead<BM, WR, KD, NS>();
   return launch_k(gemm_tiled_kernel<EPI, BM, BN, WR, KD, NS>, dim3(shared ? std::min(total, slots) : total), dim3(512),
                   (size_t)lds, s, b);
 }

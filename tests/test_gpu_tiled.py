@@ -57,6 +57,10 @@ TILES = {
     "128x128": (224, 7, 2912, 1023),           # 64 x 128: 16 x 23 = 368; 256 x 128: 92
     "256x128": (128, 2, 4096, 1025),           # 5 x 32 = 160
     "256x256": (128, 2, 8192, 1985),           # 8 x 32 = 256
+    # as many chunks as the staging runs ahead of the products (3 and 5): tiles
+    # beyond the chip's places need a workgroup of their own
+    "128x128_short_k": (96, 3, 2688, 4096),    # 32 x 21 = 672 (256 x 128: 336, a last round of a third)
+    "256x128_short_k": (160, 5, 3584, 4096),   # 16 x 28 = 448
 }
 
 
