@@ -64,16 +64,24 @@ __host__ __device__ constexpr int tiled_lds_bytes() {
 }
 
 // One kilobyte from a buffer straight into LDS: lane offset voff, wave-uniform
-// offset soff, LDS byte address dst.  Inline asm, so that the compiler does not
-// see an LDS write: it would wait for every outstanding one before any LDS
-// read (it cannot tell the ring's slots apart) and empty the ring.  No register
-// is written; the kernel counts these loads itself.  A write of M0 needs one
-// wait state before the load that takes its LDS address from it.
-__device__ __forceinline__ void stage_kb(const u32x4_t& rsrc, uint32_t voff, uint32_t soff, uint32_t dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff)
-               : "m0");
+// offset soff + pos, LDS byte address slot + dst.  Inline asm, so that the
+// compiler does not see an LDS write: it would wait for every outstanding one
+// before any LDS read (it cannot tell the ring's slots apart) and empty the
+// ring.  No vector register is written; the kernel counts these loads itself.
+// Nor does the compiler see a memory instruction that reads scalar registers,
+// so the wait states that it would put before one are here: five after a vector
+// instruction that wrote one of them (v_readlane of a spilled register,
+// v_readfirstlane), which covers the one after the write of M0.  The two
+// additions are two of them and s_nop 2 is three; the sum that the load reads is
+// written by the scalar unit, which needs none.
+__device__ __forceinline__ void stage_kb(const u32x4_t& rsrc, uint32_t voff, uint32_t soff, uint32_t pos, uint32_t slot,
+                                         uint32_t dst) {
+  uint32_t off;
+  asm volatile(
+      "s_add_u32 m0, %1, %2\n\ts_add_u32 %0, %3, %4\n\ts_nop 2\n\tbuffer_load_dwordx4 %5, %6, %0 offen lds"
+      : "=&s"(off)
+      : "s"(slot), "s"(dst), "s"(soff), "s"(pos), "v"(voff), "s"(rsrc)
+      : "m0", "scc");
 }
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
 
@@ -205,8 +213,8 @@ __global__ __launch_bounds__(512, (2 * tiled_per_cu<EPI, BM, BN, KD, NS>())) voi
     const bool isA = j < LA;
     const int f = w + kTiledWaves * (isA ? j : j - LA), per = isA ? TRB : CBB;
     const uint32_t pos = KD == 1 ? ipos : min(ipos + (uint32_t)(f / per) * 1024, cur.end - 1024);
-    if (isA) stage_kb(rA, voff, cur.a[isA ? j : 0] + pos, islot + dst_of(f, TRB, 0));
-    else stage_kb(rW, voff, cur.w[isA ? 0 : j - LA] + pos, islot + dst_of(f, CBB, TRB));
+    if (isA) stage_kb(rA, voff, cur.a[isA ? j : 0], pos, islot, dst_of(f, TRB, 0));
+    else stage_kb(rW, voff, cur.w[isA ? 0 : j - LA], pos, islot, dst_of(f, CBB, TRB));
   };
   auto staged = [&]() {  // all of them are issued
     ipos += STEP;
