@@ -184,7 +184,15 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
     for (int t = 0; t < NDTU; ++t) o[qt][t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   }
 
+  // Two blocks in flight: a block's registers are refilled as soon as it is
+  // used up.  One (wide heads): they are loaded at the top.  Refilled at the
+  // end of the step, under the loop's condition, they are undefined on the way
+  // out of it, and the compiler then gave the softmax two of the fp32 form's V
+  // registers while they were still needed (a test reads the listing for that);
+  // it was also slower: d_h = 128, 256 rows of 1024 dims 5.7 us against 5.2, 8
+  // streams 13.1 against 9.8.
   for (int kb = kb0; kb < kb1; kb += GB) {
+    if (GB == 1 && kb > kb0) load_group(kb);
 #pragma unroll
     for (int b = 0; b < GB; ++b) {
       if (kb + b < kb1) {  // uniform
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(KW * 64) void attn_kernel(AttnArgs a) {
         }
         // this block's operands are used up: the block GB further on takes
         // their registers while the blocks between are worked on
-        if (kb + b + GB < kb1) {  // uniform
+        if (GB > 1 && kb + b + GB < kb1) {  // uniform
           load_kblock<T, NDC>(kop[b], kbase, kb + b + GB, dh, g, lane);
           load_vblock<T, NDT, NDTU>(vop[b], vbase, kb + b + GB, lane);
         }

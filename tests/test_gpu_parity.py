@@ -126,6 +126,26 @@ def test_attention_tunings(waves, qtiles):
         p.check_layers(lambda v: idx[v, :count[v]], f"step {t}")
 
 
+@pytest.mark.parametrize("waves", [2, 4, 8])
+@pytest.mark.parametrize("dtype,qtiles", [("bf16", 1), ("bf16", 2), ("f32", 1)])
+@pytest.mark.parametrize("dh", [32, 64, 72, 96, 128])
+def test_attention_head_widths(dh, dtype, qtiles, waves):
+    """Every head width's form of the attention, in both storage types and every
+    workgroup shape: 285 tokens are 9 key blocks, the last one partial."""
+    from paper_2607_12287_amd import incvit
+    m = synth.ModelShape(60, 76, 3, 4, 4 * dh, 1, 4, 64, dtype)
+    w = synth.make_weights(m, 1701 + dh)
+    say(f"[attn dh={dh} {dtype} qtiles={qtiles} waves={waves}] N={m.n_tokens}")
+    frames = np.random.default_rng(1710 + dh).random((2, 2, m.n_tokens, m.patch_dim), dtype=np.float32)
+    p = Pair(m, w, 2)
+    incvit._check(incvit.incvit_set_tuning(p.enc.h, attn_qtiles=qtiles, attn_waves=waves), p.enc.h)
+    p.full_encode(frames[0])
+    p.check_layers(None, "full")
+    idx, count, refreshed, res = p.step(frames[1], np.inf, [37, 5])
+    p.check_step(idx, count, refreshed, res, "step")
+    p.check_layers(lambda v: idx[v, :count[v]], "step")
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_down_projection_modes(mode, dtype):
