@@ -300,7 +300,9 @@ void incvit_graph_destroy(incvit_graph* g);
  * are known on the host, the stream has 512 tokens or more and two-tile
  * workgroups still number 256 or more).
  * attn_waves: waves per attention workgroup, splitting the stream's keys: 2, 4
- * or 8; 0 = automatic (about two 32-key blocks per wave).
+ * or 8; 0 = automatic (about two 32-key blocks per wave, 4 or 8 waves; fewer,
+ * down to one, where the rows are known on the host and so many that fewer
+ * waves each still fill the chip).
  * fc2_mode: the MLP down projection of every layer but the last: 1 = K split
  * over workgroups, partial sums finished by a row kernel; 2 = whole K per
  * workgroup with the residual and the cache write in its epilogue; 0 = 2 when

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace incvit {
 
 constexpr int kMaxViews = 64;
@@ -333,7 +335,32 @@ hipError_t launch_gemm(int epi, int cols, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int expected, int rows, hipStream_t s);
 hipError_t launch_res(const ResArgs& a, int mmax, hipStream_t s);
 hipError_t launch_hsum(const HsumArgs& a, hipStream_t s);
-hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, bool known, hipStream_t s);
+hipError_t launch_attn(const AttnArgs& a, int max_rows_per_view, int qtiles, int waves, const int* rows, hipStream_t s);
+
+// Waves per attention workgroup (16 * qtiles query rows of a head and stream).
+// Each wave takes a share of the keys, and the shares are merged through LDS.
+// While the workgroups are few, about two 32-key blocks per wave keep every
+// wave's chain short; once there are enough of them that fewer waves each still
+// give every SIMD two, a longer run per wave does without most of the merging.
+// rows: each stream's row count where the host knows it, else null (and the
+// waves stay).  The launch has as many query groups for every stream as the
+// longest one needs, so it is the workgroups that have rows which count; of
+// those that have none, which only start and end, eight count as one.
+// Measured, us per launch at 16 heads of 64: caps of 700, 300 and six of 4 (608
+// of 2816 workgroups with rows) 4 waves 26.6, 1 wave 41.4; 256 and seven of 1
+// (240 of 1024) 4 waves 6.1, 2 waves 8.6; but 1024 and 31 of 1 (1008 of 16384)
+// 4 waves 67.2, 1 wave 49.5.
+inline int attn_waves_of(int tuned, const Shape& sh, int B, int qtiles, int max_rows, const int* rows) {
+  if (tuned > 0) return tuned;
+  int kw = sh.Npad / 32 >= 16 ? 8 : 4;
+  if (!rows) return kw;
+  const int qrows = 16 * qtiles;
+  long busy = 0;
+  for (int v = 0; v < B; ++v) busy += (rows[v] + qrows - 1) / qrows;
+  const long groups = sh.H * std::max(busy, (long)B * ((max_rows + qrows - 1) / qrows) / 8);
+  while (kw > 1 && groups * (kw / 2) >= 2048) kw /= 2;
+  return kw;
+}
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_fixed_pack(const FixedPackArgs& a, hipStream_t s);
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s);

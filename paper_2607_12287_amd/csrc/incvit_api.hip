@@ -420,12 +420,15 @@ incvit_status run(incvit_handle* h, int kind, hipStream_t s, F&& launch) {
 const float* fptr(const incvit_handle* h, size_t off) { return reinterpret_cast<const float*>(h->packed + off); }
 
 // Launch the per-layer kernels for the rows of the call (row map in ws).
-// refreshed: optional output of the last layer's final LayerNorm rows.
+// view_rows: each stream's row count where the host knows it (mmax is then their
+// sum), else null.  refreshed: optional output of the last layer's final
+// LayerNorm rows.
 // With mlp_all the output projection writes the attention branch of the
 // refreshed rows into the cache, and the residual and the MLP run over every
 // row of the call (the all-rows map in ws).
 incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLayout& wl, char* ws,
-                         int max_rows_per_view, int mmax, bool exact_m, void* refreshed, hipStream_t s) {
+                         int max_rows_per_view, int mmax, const int* view_rows, void* refreshed, hipStream_t s) {
+  const bool exact_m = view_rows != nullptr;
   // GEMM row groups: when the call's row count M is known on the host (a full
   // encode, or a pure top-k step where M is the sum of the caps), one 32-row
   // block per workgroup (up to 8 groups); otherwise one group, which loops over
@@ -601,7 +604,7 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
       aa.qmax = wl.Mpad - 1;
       aa.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)sh.dh));
       const int qtiles = attn_qtiles_of(h->attn_qtiles, B, sh.H, sh.N, max_rows_per_view, exact_m);
-      if ((st = run(h, INCVIT_K_ATTN, s, [&] { return launch_attn(aa, max_rows_per_view, qtiles, h->attn_waves, exact_m, s); })) != INCVIT_OK)
+      if ((st = run(h, INCVIT_K_ATTN, s, [&] { return launch_attn(aa, max_rows_per_view, qtiles, h->attn_waves, view_rows, s); })) != INCVIT_OK)
         return st;
       if ((st = gemm(G_OPROJ, INCVIT_K_OPROJ)) != INCVIT_OK) return st;
     }
@@ -715,7 +718,9 @@ incvit_status full_impl(incvit_handle* h, int32_t B, const float* patches, void*
   ra.z = ws + wl.z;
   set_all_rows(ra, sh, ws, wl, nullptr);
   if ((st = run(h, INCVIT_K_COMMIT, s, [&] { return launch_commit(ra, mmax, s); })) != INCVIT_OK) return st;
-  return run_layers(h, views, B, wl, ws, sh.N, mmax, true, refreshed, s);
+  int view_rows[kMaxViews];
+  std::fill_n(view_rows, B, sh.N);
+  return run_layers(h, views, B, wl, ws, sh.N, mmax, view_rows, refreshed, s);
 }
 
 }  // namespace
@@ -913,7 +918,7 @@ incvit_status incvit_step(incvit_handle* h, int32_t B, const float* patches, voi
   set_all_rows(ra, sh, ws, wl, sa.valid);
   if ((st = run(h, INCVIT_K_COMMIT, s, [&] { return launch_commit(ra, mmax, s); })) != INCVIT_OK) return st;
   // with the threshold disabled every stream refreshes exactly its cap
-  return run_layers(h, views, B, wl, ws, max_rows, mmax, std::isinf(tau) && tau > 0, refreshed, s);
+  return run_layers(h, views, B, wl, ws, max_rows, mmax, std::isinf(tau) && tau > 0 ? sa.cap : nullptr, refreshed, s);
 }
 
 incvit_status incvit_encode_frame(incvit_handle* h, int32_t B, const float* patches, void* const* caches,

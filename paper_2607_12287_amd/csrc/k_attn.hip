@@ -99,8 +99,9 @@ __device__ __forceinline__ void mask_v(V8<float>& v, int first_key, int N) {
 }
 
 // One workgroup: QT query tiles (16 queries each) of one head of one stream.
-// Its KW waves split the stream's key blocks into contiguous runs (about two
-// 32-key blocks per wave: 4 waves at N = 256, 8 at N = 1024), so the K/V of a
+// Its KW waves split the stream's key blocks into contiguous runs (while the
+// workgroups are few about two 32-key blocks per wave: 4 waves at N = 256, 8 at
+// N = 1024; down to one wave for all keys when they are many), so the K/V of a
 // head are pulled through the CU by several waves at once and each wave's
 // chain of dependent MFMA and softmax steps stays short, while the exchange
 // of the waves' partial results stays small; every wave processes all QT
@@ -341,25 +342,16 @@ static void launch_dh(const AttnArgs& a, int kw, dim3 grid, hipStream_t s) {
 // qtiles: 16-query tiles per workgroup (1 or 2).  One tile per workgroup
 // doubles the workgroups (and the K/V reads) for short per-stream row counts;
 // two halve the K/V traffic when there are many rows.  waves: 2, 4 or 8 per
-// workgroup; 0 = by the number of workgroups (known: every workgroup launched
-// has rows).
-hipError_t launch_attn(const AttnArgs& a0, int max_rows_per_view, int qtiles, int waves, bool known, hipStream_t s) {
+// workgroup; 0 = attn_waves_of.  rows: each stream's row count where the host
+// knows it, else null.
+hipError_t launch_attn(const AttnArgs& a0, int max_rows_per_view, int qtiles, int waves, const int* rows, hipStream_t s) {
   AttnArgs a = a0;
   if (!a.sh.dtype) qtiles = 1;
   const int qrows = 16 * qtiles;
   dim3 grid(a.sh.H, a.B, (max_rows_per_view + qrows - 1) / qrows);
   if (grid.z == 0) return hipSuccess;
   a.nspec = qtiles == 1 ? 2 : 1;
-  const int nkb = a.sh.Npad / 32;
-  // Each wave of a workgroup takes a share of the keys, and the shares are
-  // merged through LDS.  While the workgroups are few, about two key blocks per
-  // wave keep every wave's chain short; once there are enough of them that
-  // fewer waves each still give every SIMD two, a longer run per wave does
-  // without most of the merging.
-  int kw = waves > 0 ? waves : nkb >= 16 ? 8 : 4;
-  const long groups = (long)grid.x * grid.y * grid.z;
-  if (waves == 0 && known)
-    while (kw > 1 && groups * (kw / 2) >= 2048) kw /= 2;
+  const int kw = attn_waves_of(waves, a.sh, a.B, qtiles, max_rows_per_view, rows);
   if (!a.sh.dtype) launch_dh<float, 1>(a, kw, grid, s);  // fp32 operands: one tile (registers)
   else if (qtiles == 1) launch_dh<uint16_t, 1>(a, kw, grid, s);
   else launch_dh<uint16_t, 2>(a, kw, grid, s);
