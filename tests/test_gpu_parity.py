@@ -146,6 +146,28 @@ def test_attention_head_widths(dh, dtype, qtiles, waves):
     p.check_layers(lambda v: idx[v, :count[v]], "step")
 
 
+@pytest.mark.parametrize("dtype,qtiles", [("bf16", 1), ("bf16", 2), ("f32", 1)])
+@pytest.mark.parametrize("dh,heads", [(32, 8), (64, 4), (72, 4), (96, 4), (128, 4)])
+def test_attention_one_wave(dh, heads, dtype, qtiles):
+    """One wave for all keys, which the attention takes from 2048 workgroups with
+    rows on: full encodes of 64 streams of 285 tokens (9 query groups of 32 or 18
+    of 16 rows: 2304 workgroups and more), 9 key blocks, the last one partial,
+    every head width's form, against the oracle."""
+    from paper_2607_12287_amd import incvit
+    patch, gh, gw, B = 4, 15, 19, 64
+    m = synth.ModelShape(gh * patch, gw * patch, 3, patch, dh * heads, 1, heads, 64, dtype)
+    w = synth.make_weights(m, 1701 + dh)
+    say(f"[one attention wave dh={dh} {dtype} qtiles={qtiles}] N={m.n_tokens} B={B}")
+    assert heads * B * -(-m.n_tokens // (16 * qtiles)) >= 2048
+    frames = np.random.default_rng(1710 + dh).random((B, m.n_tokens, m.patch_dim), dtype=np.float32)
+    p = Pair(m, w, B, oracle_views=[0, B - 1])
+    incvit._check(incvit.incvit_set_tuning(p.enc.h, attn_qtiles=qtiles), p.enc.h)
+    p.full_encode(frames)
+    tf = p.check_layers(None, "full")
+    worst = p.check_caches("full")
+    say(f"  per-layer worst {tf:.2e}, free-running worst {worst:.2e}")
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_down_projection_modes(mode, dtype):
@@ -187,22 +209,24 @@ def test_down_projection_fused_so400m():
         say(f"  step {t}: count={count.tolist()} per-layer worst {tf:.2e}, free-running worst {worst:.2e}")
 
 
-@pytest.mark.parametrize("case", ["3x2", "4x2"])
+@pytest.mark.parametrize("case", ["1x1", "1x2", "2x4"])
 @pytest.mark.parametrize("score", ["embed", "key"])
 def test_patch16_register_tiles(case, score):
-    """Patch 16 (P = 768, 12 LDS tiles of k) through each register tile of the
-    fixed-order product that has an unrolled 12-tile form: one stream of 64
-    tokens takes 3 tokens x 2 columns per thread, 8 streams of 256 tokens at
-    D = 768 take 4 x 2 (fewer workgroup rounds); with the key score at
-    D = 768 the key projection (K = 768, 12 tiles) takes the same tile, at
-    D = 128 the tile loop.  Selection is checked bit-exactly, so the product
+    """Patch 16 (P = 768, 24 whole 32-deep chunks) through each tile per wave of
+    the fixed-order product, by the number of 16 x 16 output tiles: 64 (two
+    streams of 64 tokens, D = 128), 6144 (8 of 256, D = 768) and 16384 (16 of
+    256, D = 1024); with the key score the key projection (K = D) has as many
+    and takes the same tile.  Selection is checked bit-exactly, so the product
     must keep its fma order."""
-    if case == "3x2":
+    if case == "1x1":
         m = synth.small_model(dim=128, depth=1, heads=2, mlp=160, img=128, patch=16, dtype="bf16")
         B, views = 2, None
-    else:
+    elif case == "1x2":
         m = synth.small_model(dim=768, depth=1, heads=8, mlp=256, img=256, patch=16, dtype="bf16")
         B, views = 8, [0, 7]
+    else:
+        m = synth.small_model(dim=1024, depth=1, heads=16, mlp=256, img=256, patch=16, dtype="bf16")
+        B, views = 16, [0, 15]
     assert m.patch_dim == 768
     w = synth.make_weights(m, 1501)
     say(f"[patch 16 {case} {score}] N={m.n_tokens} D={m.dim} B={B}")
@@ -226,7 +250,8 @@ def test_gemm_column_blocks(cols, mode):
     QKV with the folded LayerNorm and the K/V scatter, output projection with
     the residual, MLP up with GELU, MLP down as K-split partial sums or whole
     K with the residual) in full encodes (8 row groups) and steps: the column
-    count changes which workgroup computes a column, never its sum order."""
+    count changes which workgroup computes a column, never its sum order.  With
+    the large-row GEMM off, which the 512 rows of the encodes would take."""
     from paper_2607_12287_amd import incvit
     m = synth.small_model(dim=256, depth=2, heads=4, mlp=512, img=64, patch=4, dtype="bf16")
     w = synth.make_weights(m, 1601)
@@ -234,7 +259,7 @@ def test_gemm_column_blocks(cols, mode):
     its = [synth.RefillRectStream(m, 1610 + v, v, 23, 29).frames(3) for v in range(2)]
     frames = [np.stack([synth.patchify(next(it), m.patch) for it in its]) for _ in range(3)]
     p = Pair(m, w, 2)
-    incvit._check(incvit.incvit_set_tuning(p.enc.h, cols=cols, fc2_mode=mode), p.enc.h)
+    incvit._check(incvit.incvit_set_tuning(p.enc.h, cols=cols, fc2_mode=mode, tiled=1), p.enc.h)
     p.full_encode(frames[0])
     p.check_layers(None, "full")
     p.check_caches("full")
