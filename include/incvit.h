@@ -319,9 +319,10 @@ void incvit_graph_destroy(incvit_graph* g);
  * tiled: the large-row GEMM of bf16 models (output tiles of 64 x 64 to 256 x
  * 256, K staged through LDS): 0 = automatic, by the call's rows where they are
  * known on the host (full encodes, pure top-k steps, the all-rows MLP), else by
- * 32 * row_groups: every GEMM from 512 known rows, the QKV and MLP up
- * projections from 192, the MLP up projection of more than 4096 columns from 96
- * (known or not); 1 = never (the weight-streaming GEMM above).
+ * 32 * row_groups: every GEMM from 512 known rows; where 64 x 64 tiles number
+ * 128 or more also the QKV and MLP up projections from 192 known rows and the
+ * MLP up projection of more than 4096 columns from 96 (known or not);
+ * 1 = never (the weight-streaming GEMM above).
  * The cols and row_groups fields do not apply to its launches; its MLP down
  * projection follows fc2_mode (1: split over K with the row kernel, 2:
  * unsplit; 0: split while its 64 x 128 tiles number fewer than 128).

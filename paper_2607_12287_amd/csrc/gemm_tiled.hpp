@@ -529,18 +529,21 @@ hipError_t launch_tiled_cfg(const GemmArgs& a, int rows, hipStream_t s) {
 // row count to tune for, `rows` the most that the call can have (they differ
 // when M is only known on the device; the kernel reads it).  us per launch on
 // weights from HBM, So400m (D 1152, F 4304) or ViT-L (D 1024, F 4096) widths:
-//   64 x 64 (one per CU, 128 KB ring) and 64 x 128 while they give at most one
-//     tile per CU, the larger of the two that does, which is bound by what a
-//     CU can stage: QKV of 256 rows 9.9 (64 x 128: 11.7), MLP up of 256 rows
-//     11.9 (64 x 64: 14.0), output projection of 1024 rows 9.0 (64 x 64: 10.5,
-//     128 x 128: 12.3), MLP down of 2048 rows 23.7 (128 x 128: 32);
-//   256 x 256 for the widest products, where it fills its last round: MLP up
-//     of 8192 rows 77 (256 x 128: 95, 128 x 128: 93), but QKV of 8192 rows,
-//     384 tiles, 73 (256 x 128: 71);
-//   256 x 128 where it gives more than half a tile per CU and its last round
-//     is full to three quarters, or is the only one: MLP down of 8192 rows 63
-//     (128 x 128: 75), QKV of 8192 rows 71 (74), MLP up of 1024 rows 22.4
-//     (24.4);
+//   64 x 64 (one per CU, 128 KB ring) while it gives at most one tile per CU,
+//     then 64 x 128 while that does: what a CU can stage bounds them, so the
+//     smaller of the two that fits one round is the faster: QKV of 256 rows 9.9
+//     (64 x 128: 11.7), MLP up of 256 rows 11.9 (64 x 64: 14.0), output
+//     projection of 1024 rows 9.0 (64 x 64: 10.5, 128 x 128: 12.3), MLP down of
+//     2048 rows 23.7 (128 x 128: 32);
+//   256 x 256 for the widest products (QKV, MLP up) where its tiles are a
+//     multiple of the CUs: MLP up of 8192 rows, 512 tiles, 77 (256 x 128: 95,
+//     128 x 128: 93), QKV of 16384 rows, 768 tiles, 110 (256 x 128: 129); QKV of
+//     8192 rows, 384 tiles in two rounds, 73 (256 x 128: 71); the numbers in
+//     between are not measured;
+//   256 x 128 where it gives more than half a tile per CU and one round, or
+//     rounds that are full to three quarters on the whole: MLP down of 8192 rows
+//     63 (128 x 128: 75), QKV of 8192 rows, 384 tiles in two rounds of 256, 71
+//     (74), MLP up of 1024 rows 22.4 (24.4);
 //   128 x 128 for the rest: QKV of 1024 rows 15.8 (64 x 128: 20), MLP up of
 //     512 rows 14.9 (64 x 128: 19.3); with at most one per CU its ring takes
 //     the whole LDS, more ahead of weights that come from HBM: QKV of 1024
@@ -555,6 +558,7 @@ hipError_t launch_tiled_epi(const GemmArgs& a, int expected, int rows, hipStream
   auto tiles = [&](int bm, int bn) { return (expected + bm - 1) / bm * ((a.Nout + bn - 1) / bn) * a.ksplit; };
   if (tiles(64, 64) <= 256) return launch_tiled_cfg<EPI, 64, 64, 2, 2, 8>(a, rows, s);
   if (tiles(64, 128) <= 256) return launch_tiled_cfg<EPI, 64, 128, 2, 2, 6>(a, rows, s);
+  // at least `quarters` quarters of the places in all rounds of t tiles
   auto full = [](int t, int quarters) { return 4 * t >= quarters * 256 * ((t + 255) / 256); };
   if constexpr (EPI == EPI_QKV || EPI == EPI_FC1) {
     const int x = tiles(256, 256);

@@ -224,7 +224,7 @@ GemmGeom gemm_geom(const Shape& sh, int kind) {
   // split over up to 4 workgroups (at least 8 chunks each), and a row kernel
   // adds the partial sums, the bias, the residual and the next LayerNorm.  The
   // output projection (K = D) is not split: its epilogue adds the residual
-  // itself and leaves the LN2 block statistics for fc1.
+  // itself.
   g.ksplit = 1;
   if (kind == G_FC2)
     g.ksplit = std::max(1, std::min(std::min(4, 256 / std::max(g.nblocks, 1)), g.kchunks / 8));
@@ -480,8 +480,12 @@ incvit_status run_layers(incvit_handle* h, const Views& views, int B, const WsLa
   // The large-row MLP down projection runs over K = F: its workgroup's chunks
   // follow one another, so while 64 x 128 tiles leave more than half of the CUs
   // idle it is split over K like the small-M form (partial sums added by the
-  // row kernel): So400m at 512 rows 11.7 + 5.8 us against 18.9, at 1024 rows
-  // 17.7 + 8.8 against 24.1.
+  // row kernel).  us inside full encodes, split + row kernel against whole K:
+  // So400m of 576 rows (81 tiles) 11.5 + 5.8 against 18.0 (the encode of 6
+  // layers 447 against 453), of 768 rows (108) 15.9 + 6.6 against 18.4 (459
+  // against 437: here the line lies too high), of 1024 rows (144) 18.3 + 8.4
+  // against 26.2 (609 against 610); ViT-L of 1024 rows (128) 14.0 + 7.8 against
+  // 17.5 (476 against 455).
   int fc2_split = 1;
   if (tiled_fc2) {
     const GemmGeom g2 = gemm_geom(sh, G_FC2);
