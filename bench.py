@@ -670,7 +670,7 @@ def summarize_full(trace_dir: str, pmc_dir: str, drive_log: str, out: str, comma
     for (_, n, v), k in zip(disp, kinds_in_order([n for _, n, _ in disp])):
         if k:
             util.setdefault(k, []).append(v)
-    for k in ("pack", "fold", "conv"):  # weight packing before the encodes
+    for k in ("pack", "fixed_pack", "fold", "conv"):  # weight packing before the encodes
         dur.pop(k, None)
     lines = [f"# full encodes of {b['config']['workload']}: {b['views']} stream(s) x {b['tokens']} tokens = {M} rows, "
              f"D={D}, F={F}, {L} layers; last of {reps} encodes",

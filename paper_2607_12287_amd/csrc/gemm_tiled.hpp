@@ -38,9 +38,10 @@
 // Measured (MI355X; us per launch and TFLOP/s, weights from HBM): MLP down of
 // 8192 rows (ViT-L) 75 -> 63 us, 1090; MLP up 106 -> 77, 890; QKV 79 -> 71, 725;
 // MLP up of 1024 rows (So400m) 28 -> 22, QKV 20.7 -> 16, of 256 rows 14 -> 9.9.
-// Staging alone runs at 41 B/clk per CU from a warm L2 and LDS reads alone at
-// 235 B/clk; the two share the LDS, and their sum is what bounds a 128 x 128
-// tile (no products: 72 of its 75 us).
+// This staging alone runs at 41 B/clk per CU from a warm L2 (a bare loop of LDS
+// DMA takes in 53, one of register loads 51: it is what the L2 delivers) and LDS
+// reads alone at 240 B/clk; their sum is what bounds a 128 x 128 tile (no
+// products: 72 of its 75 us).
 //
 // bf16 models only (fp32 models use the small-M kernel).  Results do not
 // depend on the tile shape beyond the fp32 order of the MFMA accumulation,
